@@ -310,10 +310,16 @@ k_finalize(int n, const double *__restrict__ Rt, double *__restrict__ R, float *
             }
         }
         __syncthreads();
+        // descending, the lower index first on ties, a NaN (non-finite input) behind every number: a
+        // total order, so that perm is a permutation of the columns whatever the values
         for (int c = tid; c < n; c += nth) {
+            auto key = [&](int j) { return s_sv[j] == s_sv[j] ? s_sv[j] : -1.0; };
+            const double kc = key(c);
             int rank = 0;
-            for (int j = 0; j < n; ++j)
-                rank += (s_sv[j] > s_sv[c]) || (s_sv[j] == s_sv[c] && j < c);
+            for (int j = 0; j < n; ++j) {
+                const double kj = key(j);
+                rank += (kj > kc) || (kj == kc && j < c);
+            }
             perm[rank] = c;
         }
         __syncthreads();

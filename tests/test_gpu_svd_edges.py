@@ -62,3 +62,21 @@ def test_svd_block_sweeps_in_a_graph():
         g.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(ref, out)) and int(info.item()) == 0
+
+
+@pytest.mark.parametrize("n", [3, 40, 100, 160])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_svd_of_non_finite_input(n, bad):
+    """info = -1, and singular values of NaN are ordered without reaching past the columns."""
+    import paper_1301_1071_amd as t
+    m = 3 * n + 5
+    print(f"svd non-finite n={n} {bad}", flush=True)
+    A = np.random.default_rng(n).standard_normal((m, n))
+    A[m // 2, n // 2] = bad
+    info = torch.zeros(1, dtype=torch.int32, device="cuda")
+    U, S, V = t.svd(torch.from_numpy(A).cuda(), info=info, check_info=False)[:3]
+    assert info.item() == -1
+    assert U.shape == (m, n) and S.shape == (n,) and V.shape == (n, n)
+    S = S.cpu().numpy()
+    num = S[~np.isnan(S)]
+    assert np.all(np.diff(num) <= 0) and not np.isnan(S[:len(num)]).any()
