@@ -36,12 +36,15 @@ using namespace blkpanel;
 
 constexpr int kMaxWideRows = 2048;
 
-// Shapes of the block factorization: rows up to NW RT 16, 16 NCT columns
+// Shapes of the block factorization: rows up to NW RT 16, more than 16 (NCT - 1) and up to 16 NCT
+// columns (Narrow: the last block of a width that leaves 16 or fewer)
 template <int NCT_, int RT_, int NW_> struct WideShape {
     static constexpr int NCT = NCT_, RT = RT_, NW = NW_, B = NW_ * RT_ * 16;
 };
 using Shape512 = WideShape<2, 4, 8>;
 using Shape1024 = WideShape<2, 8, 8>;
+using Narrow512 = WideShape<1, 4, 8>;
+using Narrow1024 = WideShape<1, 8, 8>;
 using Shape2048 = WideShape<1, 16, 8>;
 
 // One panel's rows and place: rows of input, scratch panel (row-major, ld n), stacked R
@@ -310,6 +313,8 @@ template <typename Tin, typename T, typename C>
 hipError_t wide_block(int64_t rows, int n, int b, int j0, int nb, const void *X, int64_t ldx,
                       void *gp, int64_t pstride, double *S, hipStream_t st)
 {
+    // every column tile holds columns, every row of the block fits: what the panel body assumes
+    if (nb <= 16 * (C::NCT - 1) || nb > 16 * C::NCT || b - j0 > C::B) return hipErrorInvalidValue;
     constexpr size_t lds = sizeof(BlkSmem<T, C::NCT, C::NW>) + sizeof(BlkTail<T, C::NCT>);
     auto kern = k_wide_block<Tin, T, C>;
     hipError_t e = ensure_dynamic_lds((const void *)kern, lds);
@@ -358,9 +363,13 @@ hipError_t factor_wide(int64_t rows, int n, int b, const void *X, int64_t ldx, v
 #define TSQR_BLK(SH)                                                                              \
     (j0 == 0 ? wide_block<Tin, T, SH>(rows, n, b, j0, nb, src, ldx, gp, pstride, S, st)                    \
              : wide_block<T, T, SH>(rows, n, b, j0, nb, src, ldx, gp, pstride, S, st))
+        // (the first block is never narrow: n > 64)
+#define TSQR_BLK_LAST(SH) wide_block<T, T, SH>(rows, n, b, j0, nb, nullptr, ldx, gp, pstride, S, st)
         if (b > 1024) e = TSQR_BLK(Shape2048);
+        else if (nb <= 16) e = height > 512 ? TSQR_BLK_LAST(Narrow1024) : TSQR_BLK_LAST(Narrow512);
         else if (height > 512) e = TSQR_BLK(Shape1024);
         else e = TSQR_BLK(Shape512);
+#undef TSQR_BLK_LAST
 #undef TSQR_BLK
         if (e != hipSuccess) return e;
         e = j0 == 0 ? wide_update<Tin, T, false>(height, rows, n, b, j0, nb, src, ldx, gp, pstride, nullptr, S, st)

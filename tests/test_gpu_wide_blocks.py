@@ -37,6 +37,29 @@ def test_wide_block_edges(m, n, panel_rows, dtype):
     assert np.linalg.norm(A - Q @ R, 2) <= tol * np.linalg.norm(A, 2)
 
 
+@pytest.mark.parametrize("m,n,panel_rows,dtype", [
+    (300, 130, 0, "f64"), (700, 144, 0, "f32"), (2100, 144, 1024, "f64"), (2100, 145, 1024, "f64"),
+    (1500, 130, 700, "f32"), (3000, 65, 0, "f64"), (6000, 80, 0, "f64"), (9000, 81, 0, "f64"),
+    (9000, 112, 0, "f64")])
+def test_last_block_of_up_to_16_columns(m, n, panel_rows, dtype):
+    """The last block's own shape (one column tile), at both row capacities, on both sides of 16
+    columns, in scratch panels and in place in the tree; equal on a second run."""
+    import paper_1301_1071_amd as t
+    tol = 1e-12 if dtype == "f64" else 1e-5
+    A = np.random.default_rng(3 * m + n).standard_normal((m, n))
+    A = A if dtype == "f64" else A.astype(np.float32)
+    print(f"last block m={m} n={n} panel_rows={panel_rows} {dtype}", flush=True)
+    Ad = torch.from_numpy(A).cuda()
+    Q, R = t.qr(Ad, panel_rows=panel_rows)
+    Q2, R2 = t.qr(Ad, panel_rows=panel_rows)
+    assert torch.equal(Q, Q2) and torch.equal(R, R2)
+    A, Q, R = A.astype(np.float64), Q.cpu().numpy().astype(np.float64), R.cpu().numpy().astype(np.float64)
+    _, Ro = oracle.tsqr(A, block_rows=1000)
+    assert np.linalg.norm(R - Ro) <= tol * np.linalg.norm(Ro)
+    assert _orth(Q) <= tol
+    assert np.linalg.norm(A - Q @ R, 2) <= tol * np.linalg.norm(A, 2)
+
+
 def test_wide_columns_without_a_reflection():
     """Upper triangular on top, zeros below: tau = 0 in every step of every block."""
     import paper_1301_1071_amd as t
