@@ -12,6 +12,7 @@
 // work-group rotates the columns of one pair of blocks in its LDS, and a round-robin over the block
 // pairs, one launch per round, makes a sweep.
 #include <algorithm>
+#include <type_traits>
 
 #include "tsqr_internal.h"
 
@@ -85,6 +86,40 @@ __device__ __forceinline__ void unit_rotation(double c, double s, double &cs, do
     sn = fma(s, e, s);
 }
 
+// Squared column norms between which the angle can be formed unscaled: products of two of them, which
+// are fourth powers of the entries, then keep clear of both ends of the range of FP64, also after the
+// rotations of a sweep have brought one down to the rounding error of another.  Zero counts as inside.
+__device__ __forceinline__ bool far_norm(double ss) { return ss != 0.0 && !(ss > 1e-80 && ss < 1e140); }
+
+// The rotation (cs, sn; rc = 1 / cos) that makes two columns orthogonal, from their squared norms al,
+// be and dot product ga; false where they are orthogonal to the tolerance already.  FAR: the
+// norms may lie far out, so the three are scaled by the power of two that brings the largest to 2^500
+// (exact: the same bits where both forms stay in range), which holds for norms up to 1e290 apart.
+// |ga| is among them because a tracked norm may have become 0.  Scaling every pair cost 2% of the SVD
+// of 60,000 x 40 and its gradient and 2.6% of the SVD of 8,000 x 160, a branch in the step as much at
+// n = 40; so the rounds exist twice.
+template <bool FAR>
+__device__ __forceinline__ bool jacobi_angle(double al, double be, double ga, double tol2, double &cs,
+                                             double &sn, double &rc)
+{
+    if constexpr (FAR) {
+        const int e = 500 - __builtin_amdgcn_frexp_exp(fmax(fmax(al, be), __builtin_fabs(ga)));
+        al = ldexp(al, e);
+        be = ldexp(be, e);
+        ga = ldexp(ga, e);
+    }
+    if (!(ga != 0.0 && ga * ga > tol2 * (al * be))) return false;
+    // tan 2 theta = 2 ga / (be - al): with h = hypot(d, g2), cos^2 = (1 + |d| / h) / 2 and
+    // sin = g2 sign(d) / (2 h cos); cos >= 1/sqrt(2), so neither cancels
+    const double d = be - al, g2 = 2.0 * ga;
+    const double rh = rsqrt_nr(fma(d, d, g2 * g2));
+    const double c2 = fma(0.5 * __builtin_fabs(d), rh, 0.5);
+    rc = rsqrt_nr(c2);
+    unit_rotation(c2 * rc, 0.5 * g2 * rh * rc, cs, sn);
+    if (d < 0.0) sn = -sn;
+    return true;
+}
+
 // One rotation of the columns p, q of G and V (LDS, even ld, a zero row below an odd n) by LANES
 // lanes (16 or 64; lane gl holds the row pairs gl + LANES j).  nrm holds the squared norms of the
 // columns: the rotation changes them by -+ t g_p . g_q, so only g_p . g_q is summed here; they are
@@ -92,7 +127,7 @@ __device__ __forceinline__ void unit_rotation(double c, double s, double &cs, do
 //
 // Bound by instruction issue (all pairs of a round share one CU, 2 to 4 waves per SIMD): hence one
 // dot instead of three, 16-byte accesses, and the angle by two reciprocal square roots.
-template <int LANES, int NC>
+template <int LANES, int NC, bool FAR>
 __device__ __forceinline__ bool rotate_pair(double *gp, double *gq, double *vp, double *vq, int ld,
                                             int gl, double *np_, double *nq_, double tol2)
 {
@@ -114,15 +149,8 @@ __device__ __forceinline__ bool rotate_pair(double *gp, double *gq, double *vp, 
         g1 = fma(x1, y[j][1], g1);
     }
     const double ga = LANES == 16 ? group16_sum(g0 + g1) : wave64_sum(g0 + g1);
-    if (!(ga != 0.0 && ga * ga > tol2 * (al * be))) return false;
-    // tan 2 theta = 2 ga / (be - al): with h = hypot(d, g2), cos^2 = (1 + |d| / h) / 2 and
-    // sin = g2 sign(d) / (2 h cos); cos >= 1/sqrt(2), so neither cancels
-    const double d = be - al, g2 = 2.0 * ga;
-    const double rh = rsqrt_nr(fma(d, d, g2 * g2));
-    const double rc = rsqrt_nr(fma(0.5 * __builtin_fabs(d), rh, 0.5));     // 1 / cos
-    double cs, sn;
-    unit_rotation(rc * fma(0.5 * __builtin_fabs(d), rh, 0.5), 0.5 * g2 * rh * rc, cs, sn);
-    if (d < 0.0) sn = -sn;
+    double cs, sn, rc;
+    if (!jacobi_angle<FAR>(al, be, ga, tol2, cs, sn, rc)) return false;
     d2_t u[NC], v[NC];
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
@@ -171,12 +199,12 @@ k_finalize(int n, const double *__restrict__ Rt, double *__restrict__ R, float *
     __shared__ double s_sv[NPAD];
     __shared__ double s_sg[NPAD];
     __shared__ int perm[NPAD];
-    __shared__ int s_zero, s_nonfinite, s_rot;
+    __shared__ int s_zero, s_nonfinite, s_rot, s_far;
 
     const int tid = threadIdx.x;
     const int nth = blockDim.x;
 
-    if (tid == 0) { s_zero = 0x7fffffff; s_nonfinite = 0; }
+    if (tid == 0) { s_zero = 0x7fffffff; s_nonfinite = 0; s_far = 0; }
     __syncthreads();
     for (int i = tid; i < n; i += nth) {
         const double rii = Rt[(int64_t)i * n + i];
@@ -224,22 +252,30 @@ k_finalize(int n, const double *__restrict__ Rt, double *__restrict__ R, float *
                     double ss = 0.0;
                     for (int i = gl; i < n; i += 16) ss = fma(gG[c * ld + i], gG[c * ld + i], ss);
                     ss = group16_sum(ss);
-                    if (gl == 0) s_sv[c] = ss;
+                    if (gl == 0) {
+                        s_sv[c] = ss;
+                        if (far_norm(ss)) s_far = 1;       // stays set: the next sweeps scale too
+                    }
                 }
                 __syncthreads();
-                // round 0 pairs position grp with np - 1 - grp; from round to round every player
-                // but number 0 moves up by one
-                int ia = grp, ib = np - 1 - grp;
+                const bool far = __builtin_amdgcn_readfirstlane(s_far) != 0;
                 bool any = false;
-                for (int round = 0; round < np - 1; ++round) {
-                    if (grp < npairs && ia < n && ib < n)
-                        any |= rotate_pair<16, NPAD / 32>(gG + ia * ld, gG + ib * ld, gV + ia * ld,
-                                                          gV + ib * ld, ld, gl, &s_sv[ia],
-                                                          &s_sv[ib], tol2);
-                    if (grp > 0) ia = ia + 1 == np ? 1 : ia + 1;
-                    ib = ib + 1 == np ? 1 : ib + 1;
-                    __syncthreads();
-                }
+                auto rounds = [&](auto FAR) {
+                    // round 0 pairs position grp with np - 1 - grp; from round to round every player
+                    // but number 0 moves up by one
+                    int ia = grp, ib = np - 1 - grp;
+                    for (int round = 0; round < np - 1; ++round) {
+                        if (grp < npairs && ia < n && ib < n)
+                            any |= rotate_pair<16, NPAD / 32, decltype(FAR)::value>(
+                                gG + ia * ld, gG + ib * ld, gV + ia * ld, gV + ib * ld, ld, gl, &s_sv[ia],
+                                &s_sv[ib], tol2);
+                        if (grp > 0) ia = ia + 1 == np ? 1 : ia + 1;
+                        ib = ib + 1 == np ? 1 : ib + 1;
+                        __syncthreads();
+                    }
+                };
+                if (far) rounds(std::true_type{});
+                else rounds(std::false_type{});
                 if (any && gl == 0) s_rot = 1;             // every writer stores the same value
                 __syncthreads();
                 if (s_rot == 0) break;
@@ -264,14 +300,8 @@ k_finalize(int n, const double *__restrict__ Rt, double *__restrict__ R, float *
                         al = group16_sum(al);
                         be = group16_sum(be);
                         ga = group16_sum(ga);
-                        if (!(ga != 0.0 && ga * ga > tol2 * (al * be))) continue;
-                        const double d = be - al, g2 = 2.0 * ga;
-                        const double rh = rsqrt_nr(fma(d, d, g2 * g2));
-                        const double c2 = fma(0.5 * __builtin_fabs(d), rh, 0.5);
-                        const double rc = rsqrt_nr(c2);
-                        double cs, sn;
-                        unit_rotation(c2 * rc, 0.5 * g2 * rh * rc, cs, sn);
-                        if (d < 0.0) sn = -sn;
+                        double cs, sn, rc;
+                        if (!jacobi_angle<true>(al, be, ga, tol2, cs, sn, rc)) continue;
                         for (int i = gl; i < n; i += 16) {
                             const double x = gp[i], y = gq[i], u = vp[i], v = vq[i];
                             gp[i] = cs * x - sn * y;
@@ -369,7 +399,7 @@ k_jacobi_block(int n, int W, int nblk, int round, int sweep, double *__restrict_
 {
     extern __shared__ __align__(16) double sm[];
     __shared__ double s_nrm[32];
-    __shared__ int s_rot;
+    __shared__ int s_rot, s_far;
     if (sweep > 0 && flags[sweep - 1] == 0) return;
     const int nbp = nblk + (nblk & 1);
     const int t = blockIdx.x;
@@ -383,6 +413,8 @@ k_jacobi_block(int n, int W, int nblk, int round, int sweep, double *__restrict_
         const int b = l < W ? b0 : b1;
         return b < nblk ? b * W + (l < W ? l : l - W) : n;
     };
+    if (tid == 0) { s_rot = 0; s_far = 0; }
+    __syncthreads();
     for (int l = w; l < nc; l += nth >> 6) {
         const int c = col(l);
         if (c >= n) continue;
@@ -394,27 +426,35 @@ k_jacobi_block(int n, int W, int nblk, int round, int sweep, double *__restrict_
             ss = fma(g, g, ss);
         }
         ss = wave64_sum(ss);
-        if (lane == 0) s_nrm[l] = ss;
+        if (lane == 0) {
+            s_nrm[l] = ss;
+            if (far_norm(ss)) s_far = 1;
+        }
     }
-    if (tid == 0) s_rot = 0;
     __syncthreads();
+    const bool far = __builtin_amdgcn_readfirstlane(s_far) != 0;
     const double tol = kJacobiTol * (double)n;
     const bool full = round == 0;
     bool any = false;
-    for (int r = 0; r < (full ? nc - 1 : W); ++r) {
-        int p, q;
-        if (full) {
-            p = rr_player(w, r, nc);
-            q = rr_player(nc - 1 - w, r, nc);
-        } else {
-            p = w;
-            q = W + (w + r >= W ? w + r - W : w + r);
+    auto rounds = [&](auto FAR) {
+        for (int r = 0; r < (full ? nc - 1 : W); ++r) {
+            int p, q;
+            if (full) {
+                p = rr_player(w, r, nc);
+                q = rr_player(nc - 1 - w, r, nc);
+            } else {
+                p = w;
+                q = W + (w + r >= W ? w + r - W : w + r);
+            }
+            if (col(p) < n && col(q) < n)
+                any |= rotate_pair<64, NC, decltype(FAR)::value>(gG + p * ld, gG + q * ld, gV + p * ld,
+                                                                 gV + q * ld, ld, lane, &s_nrm[p],
+                                                                 &s_nrm[q], tol * tol);
+            __syncthreads();
         }
-        if (col(p) < n && col(q) < n)
-            any |= rotate_pair<64, NC>(gG + p * ld, gG + q * ld, gV + p * ld, gV + q * ld, ld, lane,
-                                       &s_nrm[p], &s_nrm[q], tol * tol);
-        __syncthreads();
-    }
+    };
+    if (far) rounds(std::true_type{});
+    else rounds(std::false_type{});
     if (any && lane == 0) s_rot = 1;
     __syncthreads();
     if (s_rot == 0) return;

@@ -80,3 +80,52 @@ def test_svd_of_non_finite_input(n, bad):
     S = S.cpu().numpy()
     num = S[~np.isnan(S)]
     assert np.all(np.diff(num) <= 0) and not np.isnan(S[:len(num)]).any()
+
+
+@pytest.mark.parametrize("n", [2, 40, 100, 160])
+@pytest.mark.parametrize("e", [400, -400])
+def test_svd_scaled_by_a_power_of_two(n, e):
+    """Entries near 1e120 and 1e-120: the same factors bit for bit, the singular values scaled."""
+    import paper_1301_1071_amd as t
+    m = 2 * n + 37
+    print(f"svd scaled n={n} 2^{e}", flush=True)
+    A = workloads.spectrum_matrix(m, n, 3.0, seed=n)[0]
+    U, S, V = t.svd(torch.from_numpy(A).cuda())[:3]
+    Us, Ss, Vs = t.svd(torch.from_numpy(np.ldexp(A, e)).cuda())[:3]
+    assert torch.isfinite(S).all()
+    assert torch.equal(Us, U) and torch.equal(Vs, V)
+    assert np.array_equal(Ss.cpu().numpy(), np.ldexp(S.cpu().numpy(), e))
+
+
+@pytest.mark.parametrize("n", [2, 40, 100, 160])
+@pytest.mark.parametrize("hi,lo", [(100, 0), (80, 70), (100, -100)])
+def test_svd_of_graded_columns(n, hi, lo):
+    """Columns scaled from 1e<hi> down to 1e<lo>: orthogonal factors, and the singular values' product
+    is that of R's diagonal (each of the n values is relatively exact to n rounding errors)."""
+    import paper_1301_1071_amd as t
+    m = 3 * n + 37
+    print(f"svd graded n={n} 1e{hi}..1e{lo}", flush=True)
+    A = np.random.default_rng(n).standard_normal((m, n)) * np.logspace(hi, lo, n)
+    info = torch.zeros(1, dtype=torch.int32, device="cuda")
+    U, S, V, Q, R = (x.cpu().numpy() for x in t.svd(torch.from_numpy(A).cuda(), want_qr=True, info=info))
+    assert info.item() == 0 and np.all(S > 0) and np.all(np.diff(S) <= 0)
+    eye = np.eye(n)
+    assert np.linalg.norm(U.T @ U - eye, 2) <= 1e-12
+    assert np.abs(V.T @ V - eye).max() <= max(1e-15 * n, 1e-14)
+    assert np.linalg.norm((A - (U * S) @ V.T) / S[0], 2) <= 1e-12
+    assert abs(np.log(S).sum() - np.log(np.diag(R)).sum()) <= 1e-12 * n
+
+
+def test_svd_of_two_columns_apart():
+    """Norms 1e10 apart at 1e80: both values against the closed form of R's in 60 digits."""
+    import decimal
+    import paper_1301_1071_amd as t
+    rng = np.random.default_rng(7)
+    A = rng.standard_normal((4000, 2)) * np.array([1e80, 1e70])
+    U, S, V, Q, R = (x.cpu().numpy() for x in t.svd(torch.from_numpy(A).cuda(), want_qr=True))
+    with decimal.localcontext(decimal.Context(prec=60)):
+        a, b, c = (decimal.Decimal(float(x)) for x in (R[0, 0], R[0, 1], R[1, 1]))
+        f, d = a * a + b * b + c * c, a * c
+        s0 = ((f + (f * f - 4 * d * d).sqrt()) / 2).sqrt()
+        ref = [float(s0), float(d / s0)]
+    assert np.abs(S / ref - 1).max() <= 1e-14
