@@ -153,6 +153,13 @@ k_apply_wide(int64_t rows, int n, int b, const T *q1, int64_t ldq, const T *q1b,
             const int gl = g < ng1 ? g : g - ng1;
             const int hs = min(kGroup, steps / 2 - kGroup * gl);
             const T *ws = wk + (size_t)(2 * kGroup * gl + (g < ng1 ? 0 : steps)) * NT * 64;
+            // each block of products ends with 20 wait states: an FP64 result may be read by the vector
+            // unit 19 after its product, which the compiler does not keep where the two paths meet
+            auto settle = [&] {
+#pragma unroll
+                for (int t = 0; t + 1 < NT; ++t) asm volatile("" : "+v"(acc[t]));
+                asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[NT - 1]));
+            };
             if (hs == kGroup) {
 #pragma unroll
                 for (int h = 0; h < kGroup; ++h)
@@ -161,24 +168,21 @@ k_apply_wide(int64_t rows, int n, int b, const T *q1, int64_t ldq, const T *q1b,
 #pragma unroll
                         for (int t = 0; t < NT; ++t)
                             acc[t] = M::run(cur[h][e], ws[((2 * h + e) * NT + t) * 64], acc[t]);
+                settle();
             } else {
 #pragma unroll
                 for (int h = 0; h < kGroup; ++h)
-                    if (h < hs)
+                    if (h < hs) {
 #pragma unroll
                         for (int e = 0; e < 2; ++e)
 #pragma unroll
                             for (int t = 0; t < NT; ++t)
                                 acc[t] = M::run(cur[h][e], ws[((2 * h + e) * NT + t) * 64], acc[t]);
+                        settle();
+                    }
             }
         }
-        // columns below k0 go to out0, the rest to out1 (shifted by k0); the products' results are
-        // settled first, since the loop above ends on more than one path
-#pragma unroll
-        for (int t = 0; t < NT; ++t) asm volatile("" : "+v"(acc[t]));
-        asm volatile("s_nop 15\n\ts_nop 3");
-#pragma unroll
-        for (int t = 0; t < NT; ++t) asm volatile("" : "+v"(acc[t]));
+        // columns below k0 go to out0, the rest to out1 (shifted by k0)
         const int cnt = min(16, nr - blk * 16);
         To *const o0 = out0 + (rb + blk * 16) * ld0;
         To *const o1 = out1 ? out1 + (rb + blk * 16) * ld1 : o0;

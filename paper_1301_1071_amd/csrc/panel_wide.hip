@@ -202,7 +202,6 @@ k_wide_update(int64_t rows, int n, int b, int j0, int nb, int64_t panels, int st
 #pragma unroll
             for (int a = 0; a < NV; ++a) acc[0][a] = K::mfma(v[a][i], P[rt][i], acc[0][a]);
     }
-    mfma_settle(acc, 0);
 #pragma unroll
     for (int a = 0; a < NV; ++a)
 #pragma unroll
@@ -246,7 +245,6 @@ k_wide_update(int64_t rows, int n, int b, int j0, int nb, int64_t panels, int st
                 const T av = FORMQ ? sm.t[16 * w + lc][kk] : sm.t[kk][16 * w + lc];
                 y = K::mfma(av, sm.w[k][(4 * q + lr) * 16 + lc], y);
             }
-        mfma_settle(y);
 #pragma unroll
         for (int i = 0; i < 4; ++i) sm.y[16 * w + K::rit(lr, i)][lc] = -y[i];
     }
@@ -269,8 +267,6 @@ k_wide_update(int64_t rows, int n, int b, int j0, int nb, int64_t panels, int st
 #pragma unroll
         for (int q = 0; q < 4 * NV; ++q) P[rt] = K::mfma(a[q], yb[q], P[rt]);
     }
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) mfma_settle(P[rt]);
     auto store_a = [&](T *dst) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
