@@ -269,12 +269,14 @@ tsqr_status tsqr_qr_batched(tsqr_batch_plan plan, const void *const *d_A, void *
 
 /*
  * Panel-height table used by batched plans, one entry per (dtype, width class n <= 4, 8, 16,
- * 32, 64).  Each class has up to three variants of the blocked panel kernel, the same heights
- * for FP64 and FP32: 0 = default (384 rows for n <= 32, 256 above), 1 = half the row tiles per
- * wave (half height), 2 = 512 rows (n <= 16 only).  tsqr_tune_variants lists their heights for
- * width n (0 = not usable: a panel must hold at least 3n rows, or the variant repeats the
- * default).  The autotuner (paper_1301_1071_amd/autotune.py) times them and records its choice
- * with tsqr_tune_set.  Set the table before creating plans; it is process-wide.
+ * 32, 64).  The variants of the blocked panel kernel, the same heights for FP64 and FP32: 0 = 384
+ * rows for n <= 32, 256 above; 1 = half the row tiles per wave (half height); 2 = 512 rows (n <= 16
+ * only); 3 = 512 rows on eight waves (n > 32 only).  Unset entries are 0 for n <= 32 and 3 above.
+ * tsqr_tune_variants lists their heights for width n (0 = not usable: a panel must hold at least
+ * 3n rows, or the variant repeats variant 0): three entries for n <= 32, four above.  The tree
+ * levels of a plan use the FP64 entry.  The autotuner (paper_1301_1071_amd/autotune.py) times them
+ * and records its choice with tsqr_tune_set.  Set the table before creating plans; it is
+ * process-wide.
  */
 tsqr_status tsqr_tune_set(int32_t dtype, int64_t n, int32_t variant);
 tsqr_status tsqr_tune_get(int32_t dtype, int64_t n, int32_t *variant, int32_t *panel_rows);

@@ -67,10 +67,11 @@ __device__ __forceinline__ int find_task(const Task *__restrict__ t, int nt, int
 }
 
 // Panels of the batched form: the blocked kernel, variant V of the width class NCT
-// (V = 0 default height, 1 = half the row tiles per wave, 2 = 512 rows for n <= 16; kTall = 512 rows on
-// eight waves above n = 32, outside the tuned table: taken where no height is asked for, because its
-// tree is half as tall as 256-row panels' and their level 0 is no faster)
-constexpr int kTall = 3;
+// (V = 0: 384 rows for n <= 32, 256 above; 1 = half the row tiles per wave; 2 = 512 rows for n <= 16;
+// kTall = 512 rows on eight waves above n = 32, the choice there unless the table says otherwise: its
+// tree is half as tall as 256-row panels' and its level 0 no slower (64 matrices of 2,000 to 200,000
+// rows x 64: 6.85 ms against 8.17, in FP32 4.66 against 6.00))
+constexpr int kTall = 3, kVariants = 4;
 template <int NCT, int V> struct BlkShapeB {
     static constexpr int NW = (V == kTall) ? 8 : 4;
     static constexpr int RT0 = (NCT <= 2) ? 6 : 4;
@@ -145,10 +146,10 @@ k_finalize_batched(const FinalTask *__restrict__ tasks, void *const *Rout, char 
 }
 
 // ---- autotuned panel heights -----------------------------------------------------------------
-// Variant (0, 1, 2) of the register panel per (dtype, width class); set by tsqr_tune_set.
+// Variant (0 .. 3) of the register panel per (dtype, width class); set by tsqr_tune_set.
 constexpr int kClasses = 5;   // n <= 4, 8, 16, 32, 64
 std::mutex g_tune_mu;
-int g_tune[2][kClasses] = {{0, 0, 0, 0, 0}, {0, 0, 0, 0, 0}};
+int g_tune[2][kClasses] = {{0, 0, 0, 0, kTall}, {0, 0, 0, 0, kTall}};
 
 int width_class(int64_t n)
 {
@@ -174,14 +175,21 @@ int batch_panel_rows(int64_t n, int dtype, int v)
 }
 
 // A variant is usable for width n if its panels shrink every tree level (b >= 3n) and it
-// differs from the default height (variant 2 only exists for n <= 16 in FP64).
+// differs from variant 0's height (variant 2 only exists for n <= 16, kTall only above 32).
 bool variant_ok(int64_t n, int dtype, int v)
 {
-    if (v < 0 || v > 2) return false;
+    if (v < 0 || v >= kVariants || (v == kTall && n <= 32)) return false;
     if (v > 0 && batch_panel_rows(n, dtype, v) == batch_panel_rows(n, dtype, 0)) return false;
     return batch_panel_rows(n, dtype, v) >= 3 * n;
 }
 
+// The table's choice for width n (the class's entry may be unusable for it)
+int tuned_variant(int64_t n, int dtype)
+{
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    const int v = g_tune[dtype][width_class(n)];
+    return variant_ok(n, dtype, v) ? v : n > 32 ? kTall : 0;
+}
 
 // ---- launch dispatch on the width class and variant ----------------------------------------
 template <typename T, int NCT, int V>
@@ -295,9 +303,7 @@ tsqr_status tsqr_tune_get(int32_t dtype, int64_t n, int32_t *variant, int32_t *p
         !variant || !panel_rows)
         return TSQR_ERR_INVALID_ARG;
     const int dt = dtype == TSQR_DTYPE_F32 ? F32 : F64;
-    std::lock_guard<std::mutex> lk(g_tune_mu);
-    int v = g_tune[dt][width_class(n)];
-    if (!variant_ok(n, dt, v)) v = 0;
+    const int v = tuned_variant(n, dt);
     *variant = v;
     *panel_rows = batch_panel_rows(n, dt, v);
     return TSQR_OK;
@@ -311,7 +317,7 @@ tsqr_status tsqr_tune_variants(int32_t dtype, int64_t n, int32_t max, int32_t *p
         return TSQR_ERR_INVALID_ARG;
     const int dt = dtype == TSQR_DTYPE_F32 ? F32 : F64;
     int c = 0;
-    for (int v = 0; v <= 2; ++v) {
+    for (int v = 0; v < (n > 32 ? kVariants : kTall); ++v) {
         const int b = variant_ok(n, dt, v) ? batch_panel_rows(n, dt, v) : 0;
         if (c < max) panel_rows[c] = b;
         ++c;
@@ -345,17 +351,14 @@ tsqr_status tsqr_batch_plan_create(int32_t batch, const int64_t *m, const int64_
     // explicit height picks the level-0 variant with that height
     auto pick_variant = [&](int64_t w, int ldt, bool explicit_rows, int *v) -> tsqr_status {
         if (explicit_rows && opts && opts->panel_rows > 0) {
-            for (int c = 0; c <= 2; ++c)
+            for (int c = 0; c < kVariants; ++c)
                 if (variant_ok(w, ldt, c) && batch_panel_rows(w, ldt, c) == opts->panel_rows) {
                     *v = c;
                     return TSQR_OK;
                 }
             return TSQR_ERR_UNSUPPORTED;
         }
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        *v = g_tune[ldt][width_class(w)];
-        if (!variant_ok(w, ldt, *v)) *v = 0;
-        if (w > 32 && *v == 0) *v = kTall;
+        *v = tuned_variant(w, ldt);
         return TSQR_OK;
     };
 

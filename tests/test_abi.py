@@ -200,6 +200,33 @@ def test_tune_table_queries():
     assert rows.value > 0
 
 
+@pytest.mark.parametrize("dt", [0, 1])
+def test_tune_table_says_what_plans_run(dt):
+    """Above 32 columns both heights are variants: 256 rows (0) and the 512 (3) of a plan that asks for
+    none, which is also what the table reports when nothing was set; 512 is no variant of n <= 32
+    under that number."""
+    L = lib()
+    buf, c = (ctypes.c_int32 * 8)(), ctypes.c_int32()
+    v, rows = ctypes.c_int32(), ctypes.c_int32()
+    for n in (33, 64):
+        assert L.tsqr_tune_variants(dt, n, 8, buf, ctypes.byref(c)) == 0
+        assert c.value == 4 and (buf[0], buf[2], buf[3]) == (256, 0, 512)
+        assert L.tsqr_tune_get(dt, n, ctypes.byref(v), ctypes.byref(rows)) == 0
+        assert (v.value, rows.value) == (3, 512)
+        assert L.tsqr_tune_set(dt, n, 0) == 0
+        assert L.tsqr_tune_get(dt, n, ctypes.byref(v), ctypes.byref(rows)) == 0
+        assert (v.value, rows.value) == (0, 256)
+        assert L.tsqr_tune_set(dt, n, 3) == 0
+        assert L.tsqr_tune_set(dt, n, 4) == 1 and L.tsqr_tune_set(dt, n, 2) == 1
+    # an entry that a width of its class cannot use: that width's default
+    assert L.tsqr_tune_set(dt, 33, 1) == 0
+    assert L.tsqr_tune_get(dt, 64, ctypes.byref(v), ctypes.byref(rows)) == 0
+    assert (v.value, rows.value) == (3, 512) and L.tsqr_tune_set(dt, 64, 3) == 0
+    for n in (1, 16, 17, 32):
+        assert L.tsqr_tune_variants(dt, n, 8, buf, ctypes.byref(c)) == 0 and c.value == 3
+        assert buf[0] == 384 and L.tsqr_tune_set(dt, n, 3) == 1
+
+
 @pytest.mark.skipif(_gpu_visible(), reason="fake device pointers are only passed where no GPU exists")
 def test_new_entry_points_reject_bad_arguments_without_gpu():
     """tsqr_svd_f32, the refined precision on FP32 entry points, and the metric Gram."""

@@ -138,3 +138,32 @@ def test_batch512_full_size():
         assert np.all(np.diag(Rh) > 0) and np.all(np.tril(Rh, -1) == 0)
     for k in np.random.default_rng(0).choice(len(mats), 12, replace=False):
         check_fp64(mats[k], out[k][0].cpu().numpy(), out[k][1].cpu().numpy())
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_table_heights_above_32_columns(dtype):
+    """The default plan above 32 columns is the one of panel_rows=512 bit for bit; with the table set to
+    256 rows, level 0 and the tree run 256-row panels, and the result differs in rounding only."""
+    m = t()
+    tol = 1e-12 if dtype == torch.float64 else 1e-5
+    mats = mixed_batch(31, 6, 3000, 20_000, [33, 64])
+    As = [torch.from_numpy(A).to(DEV, dtype) for A in mats]
+    base = m.qr_batched(As)
+    tall = m.qr_batched(As, panel_rows=512)
+    assert all(torch.equal(a, b) for x, y in zip(base, tall) for a, b in zip(x, y))
+    assert m.tune_get(dtype, 64) == (3, 512) and m.tune_get(torch.float64, 64) == (3, 512)
+    sizes = []
+    try:
+        for v in (3, 0):
+            m.tune_set(dtype, 64, v)
+            m.tune_set(torch.float64, 64, v)
+            sizes.append(m.BatchPlan([tuple(A.shape) for A in As], dtype).workspace_bytes)
+        short = m.qr_batched(As)
+    finally:
+        m.tune_set(dtype, 64, 3)
+        m.tune_set(torch.float64, 64, 3)
+    assert sizes[1] > sizes[0]                      # 256-row panels leave twice the stacked R
+    for (Q, R), (Qs, Rs) in zip(base, short):
+        assert not torch.equal(Q, Qs)
+        assert torch.linalg.vector_norm(R - Rs) <= tol * torch.linalg.vector_norm(R)
+        assert torch.linalg.vector_norm(Q - Qs) <= tol * Q.shape[1] ** 0.5
