@@ -152,9 +152,9 @@ hipError_t launch_apply_vk(int q_dtype, int out_dtype, int64_t rows, int64_t n, 
                           int one_slice = 0)
 {
     if (n > 64)
-        return kmat ? hipErrorInvalidValue
-                    : launch_apply_wide(q_dtype, out_dtype, rows, n, b, q1, ldq, W, ldw, wstride, k,
-                                        out0, ld0, k0, out1, ld1, accumulate, st, one_slice);
+        return kmat || accumulate ? hipErrorInvalidValue
+                                  : launch_apply_wide(q_dtype, out_dtype, rows, n, b, q1, ldq, W, ldw,
+                                                      wstride, k, out0, ld0, k0, out1, ld1, st, one_slice);
     if (kmat && accumulate) return hipErrorInvalidValue;
     if (q_dtype == F64) {
         if (out_dtype == F64)

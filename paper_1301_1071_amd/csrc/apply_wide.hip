@@ -61,7 +61,7 @@ __global__ void __launch_bounds__(kWaves * 64)
 k_apply_wide(int64_t rows, int n, int b, const T *q1, int64_t ldq, const T *q1b, int64_t ldqb,
              const double *__restrict__ W, int64_t ldw, int64_t wstride, int k,
              To *out0, int64_t ld0, int k0, To *out1, int64_t ld1,
-             int accumulate, int64_t panels, int ny, int nrc)
+             int64_t panels, int ny, int nrc)
 {
     using M = MfmaW<T>;
     typedef typename M::acc_t acc_t;
@@ -195,8 +195,7 @@ k_apply_wide(int64_t rows, int n, int b, const T *q1, int64_t ldq, const T *q1b,
                 const int r = M::row(lane, i);
                 if (r >= cnt) continue;
                 To *o = j < k0 ? o0 + r * ld0 + j : o1 + r * ld1 + (j - k0);
-                if (accumulate) *o = (To)(acc[t][i] + (T)*o);
-                else *o = (To)acc[t][i];
+                *o = (To)acc[t][i];
             }
         }
     }
@@ -206,7 +205,7 @@ template <typename T, typename To, int NT>
 hipError_t apply_wide_nt(int64_t rows, int64_t n, int b, const void *q1, int64_t ldq,
                          const void *q1b, int64_t ldqb, const double *W, int64_t ldw,
                          int64_t wstride, int k, void *out0, int64_t ld0, int k0, void *out1,
-                         int64_t ld1, int acc, hipStream_t st)
+                         int64_t ld1, hipStream_t st)
 {
     const size_t lds = wide_lds(sizeof(T), n, q1b ? 2 : 1, NT);
     auto kern = k_apply_wide<T, To, NT>;
@@ -222,7 +221,7 @@ hipError_t apply_wide_nt(int64_t rows, int64_t n, int b, const void *q1, int64_t
     const int64_t blocks = ceil_div(panels, 8) * 8 * ny * nrc;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kWaves * 64), lds, st, rows, (int)n, b,
                        (const T *)q1, ldq, (const T *)q1b, ldqb, W, ldw, wstride, k, (To *)out0, ld0,
-                       k0, (To *)out1, ld1, acc, panels, ny, nrc);
+                       k0, (To *)out1, ld1, panels, ny, nrc);
     return hipGetLastError();
 }
 
@@ -231,7 +230,7 @@ constexpr size_t kMaxLds = 160 * 1024, kWideLds = 150 * 1024;
 template <typename T, typename To>
 hipError_t apply_wide_t(int64_t rows, int64_t n, int b, const void *q1, int64_t ldq, const void *q1b,
                         int64_t ldqb, const double *W, int64_t ldw, int64_t wstride, int k, void *out0,
-                        int64_t ld0, int k0, void *out1, int64_t ld1, int acc, hipStream_t st,
+                        int64_t ld0, int k0, void *out1, int64_t ld1, hipStream_t st,
                         int one_slice)
 {
     // Column slices per panel: as few as keep W's tiles within one work-group's LDS and eight
@@ -251,7 +250,7 @@ hipError_t apply_wide_t(int64_t rows, int64_t n, int b, const void *q1, int64_t 
 #define TSQR_NT(NT)                                                                               \
     case NT:                                                                                      \
         return apply_wide_nt<T, To, NT>(rows, n, b, q1, ldq, q1b, ldqb, W, ldw, wstride, k, out0, \
-                                        ld0, k0, out1, ld1, acc, st)
+                                        ld0, k0, out1, ld1, st)
     switch (nt_of(ny)) {
         TSQR_NT(1);
         TSQR_NT(2);
@@ -271,11 +270,11 @@ hipError_t apply_wide_t(int64_t rows, int64_t n, int b, const void *q1, int64_t 
 hipError_t launch_apply_wide(int q_dtype, int out_dtype, int64_t rows, int64_t n, int b,
                              const void *q1, int64_t ldq, const double *W, int64_t ldw,
                              int64_t wstride, int k, void *out0, int64_t ld0, int k0, void *out1,
-                             int64_t ld1, int accumulate, hipStream_t st, int one_slice)
+                             int64_t ld1, hipStream_t st, int one_slice)
 {
     if (n < 2 || n > kNmaxWide) return hipErrorInvalidValue;
 #define TSQR_ARGS                                                                                     \
-    rows, n, b, q1, ldq, nullptr, 0, W, ldw, wstride, k, out0, ld0, k0, out1, ld1, accumulate, st, one_slice
+    rows, n, b, q1, ldq, nullptr, 0, W, ldw, wstride, k, out0, ld0, k0, out1, ld1, st, one_slice
     if (q_dtype == F64)
         return out_dtype == F64 ? apply_wide_t<double, double>(TSQR_ARGS)
                                 : apply_wide_t<double, float>(TSQR_ARGS);
@@ -299,7 +298,7 @@ hipError_t launch_gemm2(int64_t rows, int64_t n, const double *X0, int64_t ldx0,
                                 st);
     }
     return apply_wide_t<double, double>(rows, n, b, X0, ldx0, X1, ldx1, W, n, 0, (int)n, out, ldo, (int)n,
-                                        nullptr, 0, 0, st, 0);
+                                        nullptr, 0, st, 0);
 }
 
 }  // namespace tsqr

@@ -138,7 +138,7 @@ hipError_t launch_apply_mfma(int q_dtype, int out_dtype, int64_t rows, int64_t n
 hipError_t launch_apply_wide(int q_dtype, int out_dtype, int64_t rows, int64_t n, int b,
                              const void *q1, int64_t ldq, const double *W, int64_t ldw,
                              int64_t wstride, int k, void *out0, int64_t ld0, int k0, void *out1,
-                             int64_t ld1, int accumulate, hipStream_t st, int one_slice);
+                             int64_t ld1, hipStream_t st, int one_slice);
 // out = X0 W[0 : n] (+ X1 W[n : 2 n] unless X1 is null), W with leading dimension n, n <= 128, FP64.
 hipError_t launch_gemm2(int64_t rows, int64_t n, const double *X0, int64_t ldx0, const double *X1,
                         int64_t ldx1, const double *W, double *out, int64_t ldo, hipStream_t st);
@@ -146,13 +146,14 @@ hipError_t launch_gemm2(int64_t rows, int64_t n, const double *X0, int64_t ldx0,
 // W image plus the staged blocks within one work-group's LDS.
 bool apply_one_slice_ok(int q_dtype, int out_dtype, int64_t n, int k);
 
-// General tall product on the same kernel: out = X * W (X: rows x n, row stride ldq) panel by
 // The top of a tree of several levels without an SVD, n <= 64, top panel in the V + K form (one panel
 // of `rows` rows, R~ its R): R = D R~ and info as launch_finalize, X = Q1_top D as launch_apply_mfma.
 hipError_t launch_finalize_apply(int rows, int64_t n, const double *v, const double *kmat,
                                  const double *Rt, double *R, float *Rf, int64_t ldr, double *X,
                                  int32_t *info, hipStream_t st);
-// panel (panel p of b rows uses W rows [p*wstride, +n)); accumulate != 0 adds to out.
+
+// General tall product on the same kernels: out = X * W (X: rows x n, row stride ldq) panel by
+// panel (panel p of b rows uses W rows [p*wstride, +n)); accumulate != 0 (n <= 64) adds to out.
 hipError_t launch_gemm_mfma(int q_dtype, int out_dtype, int64_t rows, int64_t n, int b,
                             const void *q1, int64_t ldq, const double *W, int64_t ldw,
                             int64_t wstride, int k, void *out0, int64_t ld0, int k0, void *out1,
