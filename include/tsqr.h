@@ -31,8 +31,8 @@
  *   - Supported: 1 <= n <= TSQR_NMAX, m >= n.  Values must be well inside the floating-point
  *     range (|a_ij| < 1e150 in FP64, < 1e17 in FP32): column norms are formed without scaling.
  *     Widths 128 < n <= TSQR_NMAX run the wide path: every level of the tree factors panels of
- *     4 n rows held in global workspace (a quarter of the rows per level, Sec. III-C), and step 3
- *     runs in column chunks of 128.  The adjoints, the comparison methods and the metrics keep
+ *     4 n rows held in global workspace (a quarter of the rows per level, Sec. III-C), in blocks of
+ *     columns.  The adjoints, the comparison methods and the metrics keep
  *     n <= TSQR_NMAX_SMALL (their n x n work runs in one work-group's LDS); the refined
  *     precision form and the batched form keep n <= 64.
  */

@@ -240,7 +240,7 @@ tsqr_status run_apply_levels(const Plan &pl, void *ws, int out_dtype, void *out0
                              int k0, void *out1, int64_t ld1, hipStream_t st,
                              void *q1_out = nullptr, bool top_done = false)
 {
-    // top_done: the top level's product is already in its X (finalize_qr)
+    // top_done: the top level's product is already in its X (launch_finalize_apply)
     const double *W = (const double *)wsp(ws, top_done ? pl.lev[pl.nlev - 1].x : pl.wtop);
     int64_t ldw = pl.k, wstride = top_done ? pl.n : 0;
     for (int L = pl.nlev - 1 - (top_done ? 1 : 0); L >= 0; --L) {

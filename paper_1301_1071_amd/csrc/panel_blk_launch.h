@@ -9,7 +9,7 @@ namespace blklaunch {
 
 using blkpanel::BlkSmem;
 
-// Panel shapes (no register spills up to 112 columns): 4 waves with 384 rows for n <= 32 (two work-groups per
+// Panel shapes (none spills registers): 4 waves with 384 rows for n <= 32 (two work-groups per
 // CU); 8 waves with 512 rows for 32 < n <= 64 and 256 rows for 64 < n <= 128 (one work-group per
 // CU).  FP32 uses the same shapes with at most 128 registers a lane, so that four waves share a SIMD
 // (3,000,001 x 33: level 0 0.80 ms at 160 registers, one work-group per CU).
@@ -18,11 +18,11 @@ template <typename T, int NCT> struct BlkShape {
     static constexpr int RT = (NCT <= 2) ? 6 : ((NCT <= 4) ? 4 : 2);
     static constexpr int B = NW * RT * 16;
     static constexpr size_t LDS = sizeof(BlkSmem<T, NCT, NW>);
-    // with the STORE_VK tail (n <= 64)
+    // with the V + K tail (n <= 64)
     static constexpr size_t LDS_VK = LDS + sizeof(blkpanel::BlkTail<T, NCT>);
 };
 
-// VK: kout != nullptr selects the STORE_VK tail (q1 receives V, kout the panels' K); otherwise
+// VK: kout != nullptr selects the V + K form (q1 receives V, kout the panels' K); otherwise
 // q1 receives the explicit Q1 (or nothing when null).
 template <typename Tin, typename T, int NCT, bool VK>
 __global__ void __launch_bounds__((NCT <= 2) ? 256 : 512, (sizeof(T) == 4) ? 4 : (NCT <= 2) ? 2 : 1)

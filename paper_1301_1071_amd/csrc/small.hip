@@ -471,6 +471,10 @@ k_jacobi_block(int n, int W, int nblk, int round, int sweep, double *__restrict_
 
 // Sweeps run by the block kernel before k_finalize takes over (which finishes what has not
 // converged by then, up to kMaxSweeps): the graded and Gaussian triangles of the tests need 7 to 11.
+// All their rounds are enqueued, whatever the matrix needs (no host read, so that a call can be
+// captured): 112 launches at n = 101, 144 at 160, 304 at 300, 592 at 301, 1,008 at 512, as many graph
+// nodes, and 0.5, 0.6, 1.3, 2.6 and 3.2 ms of host time in calls of 2.2, 3.6, 10.1, 9.7 and 22 ms on
+// 2,000 rows.  At 8,000 x 160 a working round takes 31 us (a sweep's first 54), one after convergence 2.3.
 constexpr int kBlockSweeps = 16;
 
 hipError_t launch_jacobi_blocks(int n, const double *Rt, double *G, double *Vw, int32_t *flags,
